@@ -170,9 +170,9 @@ enum {
  * e2m1 values of MXFP4) by activations split into a bfloat16 high part and a
  * bfloat16 low part, accumulating in float32; Q8_0 up to LW_GEMV_MAX_TOK
  * tokens into three parts, which hold all 24 bits. f16 weights on the matrix
- * cores are multiplied as they are by activations in two f16 parts (22
- * significant bits, after an exact power-of-two scaling per token and 64
- * elements); results that are not finite are formed in float32. Every path's
+ * cores are split exactly into two bfloat16 parts and multiplied by activations
+ * in three; results that are not finite, or below 2^-80, are formed in float32.
+ * Every path's
  * error relative to sum_k |w * x| stays below 1e-4.
  */
 LW_API int lw_matvec(int fmt, const void* W, const float* x, float* y,

@@ -72,10 +72,10 @@ def test_rows_of_several_matrices(oracle_mod, fmt):
 @pytest.mark.gpu
 @pytest.mark.parametrize("n_tok", [5, 40])
 def test_f16_keeps_float32(n_tok):
-    """f16 weights: float32 activations in two f16 parts, so the error stays
-    that of float32 sums: 22 significant bits a product (2^-23 of |w x|) and
-    float32 additions of at most K terms, taken here as 2^-20 sum |w x|, also
-    for subnormal weights and activations 2^+-40 apart in different tokens."""
+    """f16 weights: float32 activations in three bf16 parts, so the error stays
+    that of float32 sums of at most K terms, taken here as 2^-20 sum |w x|,
+    also for subnormal weights and activations 2^+-40 apart in different
+    tokens."""
     import torch
     M, K = 50, 2048
     rng = np.random.default_rng(75)
@@ -84,6 +84,52 @@ def test_f16_keeps_float32(n_tok):
     x = rng.standard_normal((n_tok, K)).astype(np.float32)
     x[1] *= np.float32(2.0 ** 40)
     x[2] *= np.float32(2.0 ** -40)
+    y = binding.matvec(F16, to_gpu(w.reshape(-1).view(np.uint8)), to_gpu(x), M, K)
+    torch.cuda.synchronize()
+    w64, x64 = w.astype(np.float64), x.astype(np.float64)
+    assert (np.abs(y.cpu().numpy() - x64 @ w64.T) <= 2.0 ** -20 * (np.abs(x64) @ np.abs(w64).T)).all()
+
+
+# one row tile (two token counts), two and four, with 16 and 32 tokens
+F16_TILES = [(50, 2048, 5), (50, 1024, 20), (6200, 256, 33), (12300, 256, 37), (12300, 512, 16), (12300, 2048, 4)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,n_tok", F16_TILES)
+def test_f16_all_bits(M, K, n_tok):
+    """A weight row of zeros and a single one, or the smallest subnormal,
+    returns its activations bit for bit: all 24 bits, whatever their size and
+    that of the others (the smallest weight's outputs stay above 2^-126)."""
+    import torch
+    assert binding.kernel_name(F16, M, K, n_tok).count(",") == 4
+    rng = np.random.default_rng(77)
+    w = np.zeros((M, K), np.float16)
+    col = rng.integers(0, K, M)
+    w[np.arange(M), col] = np.where(np.arange(M) % 2, 1, 2.0 ** -24)
+    x = rng.standard_normal((n_tok, K)).astype(np.float32) * np.exp2(rng.integers(-60, 1, (n_tok, K))).astype(np.float32)
+    x[1] = rng.standard_normal(K).astype(np.float32) * np.float32(2.0 ** -95)
+    x[2] *= np.float32(2.0 ** 120)
+    y = binding.matvec(F16, to_gpu(w.reshape(-1).view(np.uint8)), to_gpu(x), M, K)
+    torch.cuda.synchronize()
+    assert (y.cpu().numpy() == x[:, col] * w.astype(np.float32)[np.arange(M), col]).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("big", [1e5, 1e9, 1e12, 1e30, 3e38])
+@pytest.mark.parametrize("M,K,n_tok", F16_TILES)
+def test_f16_range_within_a_chunk(M, K, n_tok, big):
+    """Large activations that meet zero weights take nothing from the others'
+    products: float32 sums of at most K terms, 2^-20 sum |w x|. Every other
+    token has one in each 64 columns, the last also a subnormal one beside."""
+    import torch
+    rng = np.random.default_rng(78)
+    w = (rng.standard_normal((M, K)) * 0.02).astype(np.float16)
+    x = rng.standard_normal((n_tok, K)).astype(np.float32)
+    at = np.arange(0, K, 64) + rng.integers(0, 64, K // 64)
+    w[:, at] = 0
+    x[::2, at] = np.float32(big)
+    x[-1] = x[0]
+    x[-1, np.delete(np.arange(K), at)[::3]] = np.float32(2.0 ** -140)
     y = binding.matvec(F16, to_gpu(w.reshape(-1).view(np.uint8)), to_gpu(x), M, K)
     torch.cuda.synchronize()
     w64, x64 = w.astype(np.float64), x.astype(np.float64)
@@ -124,7 +170,7 @@ def test_routes():
     assert name(Q8_0, 2048, 2048, 5).startswith("gemv_kernel<1, 5")      # 10240 activations: the vector kernel
     assert name(Q8_0, 2048, 2048, 6) == "gemv_kernel<1, 1, 1, 4, 3>"     # three bf16 parts
     assert name(F16, 2048, 2048, 3).count(",") == 3
-    assert name(F16, 2048, 2048, 4) == "gemv_kernel<0, 1, 1, 2, 2>"
+    assert name(F16, 2048, 2048, 4) == "gemv_kernel<0, 1, 1, 2, 3>"
     assert name(Q4_0, 65536, 4096, 64) == "gemm32_kernel<2, 8>"         # tall: the tiled kernel
     assert name(Q4_0, 1024, 4096, 64) == "gemm32_kernel<2, 2, 1, 16, 2>"
     assert name(Q4_0, 1024, 4096, 129) == "gemm32_kernel<2, 8>"
