@@ -168,10 +168,10 @@ enum {
  * reduced-precision activations) on the VALU paths. The matrix-core paths of
  * the quantized formats multiply exact bfloat16 codes (integer codes, or the
  * e2m1 values of MXFP4) by activations split into a bfloat16 high part and a
- * bfloat16 low part, accumulating in float32; Q8_0 up to LW_GEMV_MAX_TOK
- * tokens into three parts, which hold all 24 bits. f16 weights on the matrix
- * cores are split exactly into two bfloat16 parts and multiplied by activations
- * in three; results that are not finite, or below 2^-80, are formed in float32.
+ * bfloat16 low part, accumulating in float32. f16 weights and, up to
+ * LW_GEMV_MAX_TOK tokens, Q8_0 keep float32's precision there: activations in
+ * three bfloat16 parts, which hold all 24 bits, f16 weights exactly in two;
+ * results that are not finite, or below 2^-80, are formed in float32.
  * Every path's
  * error relative to sum_k |w * x| stays below 1e-4.
  */

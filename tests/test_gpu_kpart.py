@@ -161,6 +161,30 @@ def test_f16_infinities_and_nan(n_tok):
     assert np.isfinite(y[fine]).all() and np.abs(y[fine] - ref[fine]).max() < 1e-4
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,n_tok", [(40, 2304, 6), (40, 6400, 3), (12300, 2048, 8)])
+def test_q8_0_infinities_and_range(M, K, n_tok):
+    """Q8_0 up to 8 tokens: infinite and NaN activations, and finite ones above
+    bfloat16's largest, give what float32 products and sums give; tiny ones keep
+    their bits. Rows 1 and up hold one code each, so that they are exact."""
+    import torch
+    assert binding.kernel_name(Q8_0, M, K, n_tok).endswith(", 3>")
+    rng = np.random.default_rng(79)
+    q = np.zeros((M, K), np.int8)
+    col = rng.integers(256, K, M)
+    q[np.arange(M), col] = 1
+    q[0] = 1
+    W = layout.pack_q8_0(q.reshape(-1), np.ones(M * K // 32, np.float16))
+    x = rng.standard_normal((n_tok, K)).astype(np.float32)
+    x[0, 3], x[1, 4] = np.inf, np.float32(-3.4e38)
+    x[2] *= np.float32(2.0 ** -110)
+    y = binding.matvec(Q8_0, to_gpu(W), to_gpu(x), M, K)
+    torch.cuda.synchronize()
+    y = y.cpu().numpy()
+    assert y[0, 0] == np.inf and y[1, 0] == np.float32(-3.4e38)
+    assert np.isnan(y[0, 1:]).all() and (y[1:, 1:] == x[1:, col[1:]]).all()  # inf x 0: NaN
+
+
 def test_routes():
     """Where the rule draws its lines, and the launches of each side (no GPU)."""
     name, count = binding.kernel_name, binding.launch_count
