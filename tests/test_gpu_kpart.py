@@ -43,6 +43,26 @@ def test_few_tokens(oracle_mod, fmt, M, K, n_tok):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("fmt", [f for f in sorted(layout.FORMAT_NAMES) if f not in (F16, Q8_0)])
+@pytest.mark.parametrize("M,K,n_tok", [(100, 2048, 8), (100, 2048, 13), (100, 2048, 40), (6200, 768, 12), (3100, 768, 40)])
+def test_offsets_cancel(oracle_mod, fmt, M, K, n_tok):
+    """Activations of 16 bits in +-[1, 2): two bf16 parts hold them whole, and a
+    block's product less its offset fits in float32, so what is left is the
+    rounding of K / 32 block values: at most 8 additions a wave and 8 waves, each
+    2^-24 of a partial sum that grows as the root, 2^-24 * 2, and again for the
+    formats with a term of their own for the minimum."""
+    import torch
+    assert binding.kernel_name(fmt, M, K, n_tok).count(",") == 4
+    rng = np.random.default_rng([80, fmt])
+    W = synth.gen_packed(fmt, M * K, rng)
+    x = (rng.integers(2 ** 15, 2 ** 16, (n_tok, K)) * 2.0 ** -15 * rng.choice([-1, 1], (n_tok, K))).astype(np.float32)
+    y = binding.matvec(fmt, to_gpu(W), to_gpu(x), M, K)
+    torch.cuda.synchronize()
+    ref = x.astype(np.float64) @ oracle_mod.dequant(fmt, W, M * K).reshape(M, K).astype(np.float64).T
+    assert np.linalg.norm(y.cpu().numpy() - ref) <= 2 * 2 * 2.0 ** -24 * np.linalg.norm(ref)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("K", [768, 1280])
 def test_q8_0_half_super_blocks(oracle_mod, K):
     """Q8_0 with 64 rows a workgroup: units of half a super-block, fewer than
