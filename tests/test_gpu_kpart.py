@@ -8,7 +8,7 @@ import gate
 from gpu_util import to_gpu
 from parity import Ref, kernel_of
 from paper_2605_20706_amd import binding, layout, synth
-from paper_2605_20706_amd.layout import F16, Q4_0, Q4_K, Q8_0
+from paper_2605_20706_amd.layout import F16, MXFP4, Q4_0, Q4_1, Q4_K, Q5_0, Q5_1, Q5_K, Q6_K, Q8_0
 
 # (M, K, n_tok): one row; a ragged row tile; 9 super-blocks over 8 waves; a
 # token tile and one more token; 32 tokens and one more; the most tokens
@@ -220,3 +220,21 @@ def test_routes():
     assert name(Q4_0, 1024, 4096, 129) == "gemm32_kernel<2, 8>"
     assert name(Q4_K, 1000, 1 << 24, 12) == "gemm32_kernel<3, 8>"       # beyond 32-bit lane offsets
     assert count(F16, 2048, 2048, 34) == 2 and count(F16, 4096, 4096, 34) == 1
+
+
+def test_routes_of_few_tokens():
+    """Up to 8 tokens: one round of workgroups, and not a second one with little
+    in it; long K over few rows stays with the pair-step kernel (no GPU)."""
+    def here(fmt, M, K, n_tok):
+        return binding.kernel_name(fmt, M, K, n_tok).count(",") == 4
+    for n_tok in (6, 7):
+        for fmt in (Q4_0, Q4_K, Q4_1):
+            assert not here(fmt, 4096, 14336, n_tok) and not here(fmt, 3000, 12288, n_tok)
+            assert here(fmt, 3000, 6144, n_tok) and here(fmt, 8192, 14336, n_tok) and not here(fmt, 10240, 4096, n_tok)
+    for n_tok in (2, 5, 8):
+        for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, MXFP4):
+            assert here(fmt, 4096, 14336, n_tok) and here(fmt, 8192, 4096, n_tok)
+            assert not here(fmt, 20000, 3072, n_tok) and not here(fmt, 9600, 11008, n_tok)
+        assert here(Q5_K, 16384, 4096, n_tok) and not here(Q5_K, 16384, 3072, n_tok)  # 12 super-blocks over 8 waves
+    assert here(Q8_0, 4096, 14336, 2) and not here(Q8_0, 512, 14336, 2) and not here(Q8_0, 6144, 4096, 2)
+    assert here(F16, 14336, 4096, 2) and not here(F16, 512, 14336, 2) and here(F16, 512, 2048, 4)
