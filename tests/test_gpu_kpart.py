@@ -43,6 +43,14 @@ def test_few_tokens(oracle_mod, fmt, M, K, n_tok):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("fmt", [f for f in sorted(layout.FORMAT_NAMES) if f != F16])
+@pytest.mark.parametrize("M,K,n_tok", [(4111, 1280, 40), (4111, 1792, 33)])
+def test_four_waves_for_five_to_seven_super_blocks(oracle_mod, fmt, M, K, n_tok):
+    """More than a round of workgroups: two a compute unit."""
+    run_check(oracle_mod, fmt, M, K, n_tok)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("fmt", [f for f in sorted(layout.FORMAT_NAMES) if f not in (F16, Q8_0)])
 @pytest.mark.parametrize("M,K,n_tok", [(100, 2048, 8), (100, 2048, 13), (100, 2048, 40), (6200, 768, 12), (3100, 768, 40)])
 def test_offsets_cancel(oracle_mod, fmt, M, K, n_tok):
