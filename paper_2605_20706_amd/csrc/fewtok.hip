@@ -458,21 +458,13 @@ hipError_t launch_tpw(RowSegs<NS> sg, const float* x, int64_t K, int64_t n_tok, 
     return hipGetLastError();
 }
 
-int cu_count_ft() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-        return 256;
-    return v;
-}
-
 // M: rows of the row space (all segments)
 template <int FMT, int NS>
 hipError_t launch_f(const RowSegs<NS>& sg, const float* x, int64_t M, int64_t K, int64_t n_tok, hipStream_t stream) {
     if (n_tok < 2 || n_tok > 8 || K % 256 || M >= ((int64_t)1 << 30) || K >= ((int64_t)1 << 30))
         return hipErrorNotSupported;
     const int nsb = (int)(K / 256);
-    const int64_t cus = cu_count_ft();
+    const int64_t cus = cu_count();
     // rows per workgroup: about M / #CU, at least 8
     int64_t G = (M + 7) / 8;
     if (G > cus) G = cus;

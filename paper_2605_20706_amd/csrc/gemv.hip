@@ -25,7 +25,6 @@
 //    with the per-group sums of x precomputed in LDS per tile.
 // Accumulation is float32 throughout; only the rounding order differs from
 // the plain definition.
-#include <atomic>
 
 #include "lw_device.hpp"
 #include "lw_internal.hpp"
@@ -1475,19 +1474,6 @@ template <int FMT, int NT>
 constexpr bool fits_one_chunk() {
     return (int64_t)NT * (kWave * Traits<FMT>::EPL * 4 + (Traits<FMT>::kGroupSums ? kWave * 4 : 0)) <=
            kLdsBytes;
-}
-
-// Compute units of the current device, looked up once per device.
-int cu_count() {
-    static std::atomic<int> cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int v = cache[dev].load(std::memory_order_relaxed);
-    if (v <= 0) {
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
-        cache[dev].store(v, std::memory_order_relaxed);
-    }
-    return v;
 }
 
 // Rows of one matrix as a one-segment row space.

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <string>
 
 #include "lw.h"
@@ -129,6 +130,19 @@ struct RowSegs {
     float* y[NS];
     int64_t off1[NS], off2[NS], off3[NS], start[NS], M[NS], wg0[NS];
 };
+
+// Compute units of the current device, looked up once per device.
+inline int cu_count() {
+    static std::atomic<int> cache[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int v = cache[dev].load(std::memory_order_relaxed);
+    if (v <= 0) {
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) v = 256;
+        cache[dev].store(v, std::memory_order_relaxed);
+    }
+    return v;
+}
 
 // Kernel launchers. Arguments are already validated; each returns the
 // hipError_t of its launch.

@@ -47,14 +47,6 @@ __device__ __forceinline__ bf16x8 biased_codes(uint32_t w) {
     return __builtin_bit_cast(bf16x8, v);
 }
 
-int cu_count_mt() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-        return 256;
-    return v;
-}
-
 // 4 x 4 transpose across the four 16-lane groups: lane (g, i) holds words
 // w0..w3 of block g of its row; afterwards word j of the result is word g of
 // block j (v_permlane32_swap, v_permlane16_swap).
@@ -378,7 +370,7 @@ hipError_t launch_rg(const uint8_t* W, const float* x, float* y, int64_t M, int6
 template <int FMT>
 hipError_t launch_f(const uint8_t* W, const float* x, float* y, int64_t M, int64_t K, int64_t n_tok,
                      const Planes& p, hipStream_t stream) {
-    const int64_t cus = cu_count_mt();
+    const int64_t cus = cu_count();
     const bool rg2 = (M + 31) / 32 >= cus;
     const int64_t wgs = rg2 ? (M + 31) / 32 : (M + 15) / 16;
     const int nw = wgs >= 2 * cus ? 4 : 8;

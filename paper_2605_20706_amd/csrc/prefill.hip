@@ -1299,14 +1299,6 @@ __global__ void zero_kernel(float* __restrict__ y, int64_t n) {
 
 }  // namespace
 
-int cu_count_pf() {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0)
-        return 256;
-    return v;
-}
-
 // Work split of a launch over `tiles` (row tile, token tile) pairs: K splits
 // on super-block boundaries, the fewest that keep the compute units (one
 // workgroup each) at least 85 % busy over the launch's rounds, else the best
@@ -1317,7 +1309,7 @@ GemmSplit plan_split(int64_t nrt, int64_t ntt, int64_t K, int64_t cus) {
     sp.ntt = ntt;
     const int nsb = (int)(K / 256);
     const int64_t tiles = nrt * ntt;
-    if (cus <= 0) cus = cu_count_pf();
+    if (cus <= 0) cus = cu_count();
     const int kmax = nsb / 4 > 1 ? nsb / 4 : 1;
     int best = 1;
     double best_eff = 0.0;
