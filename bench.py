@@ -51,8 +51,7 @@ MAX_GRAPH_NODES = 16384
 # the term mass F on top of 1e-4 per unit of A.
 C_FACTORED = 2.0 ** -17
 F32_BOUND = 1e-4
-MFMA_KERNELS = ("fewtok_kernel", "multitok_kernel", "multitok_pk_kernel", "skinny_kernel", "gemm_kernel",
-                "gemm32_kernel")
+MFMA_KERNELS = ("fewtok_kernel", "multitok_pk_kernel", "kpart_kernel", "gemm_kernel", "gemm32_kernel")
 METRIC_ATTN = "decode attention over a quantized KV cache, HBM GB/s of K and V read per decode step"
 # Llama-3-8B attention: 32 layers, 32 query heads over 8 key/value heads of 128
 ATTN_MODEL = {"n_layers": 32, "n_heads": 32, "n_kv": 8, "head_dim": 128}
@@ -333,27 +332,20 @@ def run_gpu(ws, steps, warmup, mode):
 
 
 KERNEL_SOURCES = {"gemv_kernel": "gemv.hip", "gemv1_kernel": "gemv.hip", "gemv1r_kernel": "gemv.hip",
-                  "multitok_kernel": "kpart.hip", "multitok_pk_kernel": "multitok.hip",
-                  "fewtok_kernel": "fewtok.hip", "skinny_kernel": "kpart.hip", "gemm_kernel": "prefill.hip",
-                  "gemm32_kernel": "prefill.hip", "fp4mm_kernel": "fp4mm.hip",
+                  "multitok_pk_kernel": "multitok.hip", "fewtok_kernel": "fewtok.hip", "kpart_kernel": "kpart.hip",
+                  "gemm_kernel": "prefill.hip", "gemm32_kernel": "prefill.hip", "fp4mm_kernel": "fp4mm.hip",
                   "dequant_kernel": "dequant.hip"}
-# names the kernel with K split over its waves shares; its own have five template arguments
-KPART_NAMES = ("gemv_kernel", "fewtok_kernel", "gemm_kernel", "gemm32_kernel")
-
-
-def kernel_source(kernel):
-    base = kernel.split("<")[0]
-    return "kpart.hip" if base in KPART_NAMES and kernel.count(",") == 4 else KERNEL_SOURCES[base]
 
 
 def source_hash(kernels):
     """sha256 over the sources of the given kernels (names as lw_kernel_name
-    gives them), the shared device and host headers and the C header: a stored
+    gives them), every header beside them and the C header: a stored
     HBM traffic figure is valid only for the sources it was measured on."""
     import hashlib
 
-    files = sorted({kernel_source(k) for k in kernels})
-    files = [os.path.join(CSRC, f) for f in files + ["lw_device.hpp", "lw_internal.hpp"]]
+    files = sorted({KERNEL_SOURCES[k.split("<")[0]] for k in kernels})
+    files = [os.path.join(CSRC, f) for f in files + sorted(
+        f for f in os.listdir(CSRC) if f.endswith(".hpp"))]
     files.append(os.path.join(ROOT, "include", "lw.h"))
     h = hashlib.sha256()
     for f in files:

@@ -7,8 +7,8 @@
 // registers, where its table has an entry for the shape; else one token ->
 // the VALU matrix-vector kernel with the activation in LDS; more tokens ->
 // the matrix-core kernel with K split over its waves wherever kpart_takes
-// prefers it (every format from 9 to 16 tokens, most shapes up to 64 or 128,
-// f16 at any count); else 2..8 tokens -> the few-token matrix-core kernels
+// prefers it (every quantized format from 9 to 16 tokens, most shapes up to 64
+// or 128, f16 at any count but the smallest products); else 2..8 tokens -> the few-token matrix-core kernels
 // (f16, Q8_0: the VALU kernels), and more the tiled matrix-core (prefill)
 // kernel.
 // lw_matvec_ws (a workspace) sends LW_MXFP4 prefill to the fp4 matrix cores.
@@ -52,7 +52,7 @@ hipError_t launch_family(int cand, int fmt, const uint8_t* Wb, const float* x, f
     if (cand == lw::kCandFewtok && n_tok >= 2 && n_tok <= 8) return lw::launch_fewtok(fmt, Wb, x, y, M, K, n_tok, p, s);
     if (cand == lw::kCandMultitok && lw::multitok_supported(fmt, n_tok))
         return lw::launch_multitok(fmt, Wb, x, y, M, K, n_tok, p, s);
-    if ((cand == lw::kCandKpart && n_tok >= 2) || (cand == lw::kCandMultitok && n_tok >= 9 && n_tok <= 16))
+    if (cand == lw::kCandKpart && n_tok >= 2)
         return lw::launch_kpart(fmt, 1, &Wb, &y, &M, x, K, n_tok, s);
     if (cand == lw::kCandPrefill && n_tok >= 9) return lw::launch_prefill(fmt, Wb, x, y, M, K, n_tok, p, s);
     return hipErrorNotSupported;

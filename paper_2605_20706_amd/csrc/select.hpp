@@ -36,7 +36,7 @@ enum Cand : int {
     kCandReg2_1x7_G2_D2_C1 = 24,
     kCandReg2_1x2_G8_D2_C1 = 25,
     kCandFewtok = 30,    // few-token matrix-core kernel, activations in LDS (2..8 tokens)
-    kCandMultitok = 31,  // pair-step matrix-core kernel (2..8 tokens); 9..16 tokens: as kCandKpart
+    kCandMultitok = 31,  // pair-step matrix-core kernel (2..8 tokens)
     kCandPrefill = 32,   // tiled matrix-core kernel (9 or more tokens)
     kCandKpart = 33,     // matrix-core kernel with K split over its waves (2 or more tokens)
 };

@@ -12,8 +12,7 @@ import numpy as np
 from paper_2605_20706_amd import binding
 from paper_2605_20706_amd.layout import F16, MXFP4, Q1_0, Q8_0
 
-MFMA_KERNELS = frozenset({"fewtok_kernel", "multitok_kernel", "multitok_pk_kernel", "skinny_kernel",
-                          "gemm_kernel", "gemm32_kernel"})
+MFMA_KERNELS = frozenset({"fewtok_kernel", "multitok_pk_kernel", "kpart_kernel", "gemm_kernel", "gemm32_kernel"})
 
 
 def beta_of(kernel):

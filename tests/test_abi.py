@@ -183,10 +183,10 @@ def test_kernel_selection_table(lib):
     tokens over the 4-bit formats: the matrix-core kernel with the
     activations in LDS for matrices with at least two 16-row tiles per
     workgroup (and K >= 4096 for Q4_0), else the pair-step matrix-core kernel;
-    9..16 the few-token one with two MFMAs per block; more: the tiled
-    matrix-core kernel. The formats without the pair-step kernel
-    (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, MXFP4) take the first matrix-core kernel
-    for 2..8 tokens at every shape and the tiled kernel beyond."""
+    9..16 the one with K split over its waves; more: the tiled matrix-core
+    kernel. The formats without the pair-step kernel (Q5_0, Q5_1, Q5_K, Q6_K,
+    Q2_K, MXFP4) take the kernel with K split for 2..8 tokens where its
+    workgroups are one round, else the first matrix-core kernel."""
     from paper_2605_20706_amd import synth
 
     def kind(fmt, M, K, nt):
@@ -197,7 +197,7 @@ def test_kernel_selection_table(lib):
             for nt in (1, 2, 4, 8, 12, 512):
                 name = binding.kernel_name(wl.fmt, m.M, m.K, nt)
                 assert name and re.fullmatch(r"\w+_kernel<\d+(, \d+)*>", name), (key, m, nt, name)
-                assert name.startswith(("gemv", "multitok", "fewtok", "skinny", "gemm")), name
+                assert name.startswith(("gemv", "multitok", "fewtok", "kpart", "gemm")), name
     # shapes the swept table names (profiles/sweep_select.json): see test_selection_table_matches_sweep;
     # the built-in rules elsewhere
     assert kind(Q4_K, 14336, 4096, 1) == "gemv1r_kernel"      # 8B gate: 2 chunks, many rows
@@ -207,21 +207,24 @@ def test_kernel_selection_table(lib):
     assert kind(Q4_0, 14336, 4096, 2) == "gemv1r_kernel"
     assert kind(Q4_K, 128256, 4096, 8) == "fewtok_kernel"       # lm_head: two tiles per wave
     assert kind(Q4_0, 8192, 2048, 4) == "multitok_pk_kernel"    # 1B gate Q4_0: K below 4096
-    assert kind(Q4_K, 14336, 4096, 9) == "multitok_kernel"
+    assert kind(Q4_K, 14336, 4096, 9) == "kpart_kernel"
     assert kind(Q4_0, 14336, 4096, 512) == "gemm32_kernel"
-    assert kind(Q8_0, 14336, 4096, 512) == "gemm_kernel"
+    assert kind(Q8_0, 14336, 4096, 512) == "kpart_kernel"
+    assert kind(Q8_0, 14336, 4096, 1030) == "gemm_kernel"
     assert kind(F16, 2048, 2048, 1) == "gemv1_kernel"
-    assert kind(Q8_0, 2048, 2048, 12) == "skinny_kernel"
-    assert kind(F16, 2048, 2048, 20) == "gemv_kernel"
+    assert kind(Q8_0, 2048, 2048, 12) == "kpart_kernel"
+    assert kind(F16, 2048, 2048, 20) == "kpart_kernel"
+    assert kind(F16, 2048, 2048, 3) == "gemv_kernel"
+    assert kind(Q8_0, 2048, 2048, 5) == "gemv_kernel"
     for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, 11):            # one token: the LDS kernel
         assert kind(fmt, 14336, 4096, 1) == "gemv1_kernel"
-    for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, 11):            # 2..8 tokens: the few-token matrix-core kernel
-        for nt in (2, 4, 8):
-            assert kind(fmt, 14336, 4096, nt) == "fewtok_kernel"
-        assert kind(fmt, 100, 2304, 4) == "fewtok_kernel"     # one tile, K split over the waves
-        assert kind(fmt, 4096, 14336, 8) == "fewtok_kernel"   # the 8B down projection
-    for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, 11):            # from 9 tokens: the tiled matrix cores
-        assert kind(fmt, 14336, 4096, 12) == "gemm32_kernel"
+    for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, 11):            # 2..8 tokens: K split over the waves where the
+        for nt in (2, 4, 8):                                  # row tiles are one round, else the few-token kernel
+            assert kind(fmt, 100, 2048, nt) == "kpart_kernel"
+            assert kind(fmt, 4096, 14336, nt) == "kpart_kernel"     # the 8B down projection
+            assert kind(fmt, 20000, 4096, nt) == "fewtok_kernel"
+    for fmt in (Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, 11):            # from 9 tokens, and the tiled matrix cores beyond
+        assert kind(fmt, 14336, 4096, 12) == "kpart_kernel"
         assert kind(fmt, 14336, 4096, 512) == "gemm32_kernel"
 
 
@@ -257,8 +260,8 @@ def test_edge_cases_cover_every_kernel_family(lib):
             seen.add(binding.kernel_name(fmt, M, K, nt).split("<")[0])
         for Ms, K, nt in e.EDGE_MULTI:
             seen.add(binding.kernel_name_multi(fmt, list(Ms), K, nt).split("<")[0])
-    families = {"gemv_kernel", "gemv1_kernel", "gemv1r_kernel", "fewtok_kernel", "multitok_kernel",
-                "multitok_pk_kernel", "skinny_kernel", "gemm_kernel", "gemm32_kernel"}
+    families = {"gemv_kernel", "gemv1_kernel", "gemv1r_kernel", "fewtok_kernel", "multitok_pk_kernel",
+                "kpart_kernel", "gemm_kernel", "gemm32_kernel"}
     assert families <= seen, families - seen
 
 
@@ -313,6 +316,9 @@ def test_forced_candidates_name_their_kernels(lib, monkeypatch):
     assert binding.kernel_name(Q4_0, 8200, 4096, 4).startswith("fewtok_kernel<")
     monkeypatch.setenv("LW_FORCE_CFG", "31")
     assert binding.kernel_name(Q4_0, 8200, 4096, 4).startswith("multitok")
+    monkeypatch.setenv("LW_FORCE_CFG", "33")
+    for nt in (2, 4, 12, 40):
+        assert binding.kernel_name(Q4_0, 8200, 4096, nt).startswith("kpart_kernel<")
     monkeypatch.setenv("LW_FORCE_CFG", "32")
     assert binding.kernel_name(Q4_0, 8200, 4096, 12).startswith("gemm32_kernel<")
     # a 2-chunk candidate on a 1-chunk shape: the built-in rule for one chunk

@@ -28,10 +28,10 @@ pytestmark = pytest.mark.gpu
 FMTS = [0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11]
 # (M, K, n_tok): the single-token LDS kernel; the register kernel (one chunk,
 # two tokens, seven chunks over seven waves); the pair-step and few-token
-# matrix-core kernels; the 9..16-token kernels (multitok, Q8_0 skinny, VALU
-# token blocks); prefill (gemm32 with a K split, Q8_0 gemm, token blocks).
+# matrix-core kernels; the kernel with K split over its waves at 12 and 40
+# tokens; prefill beyond its range (gemm32 and Q8_0 gemm with a K split).
 EDGE_SHAPES = [(300, 2304, 1), (3000, 2048, 1), (2000, 2048, 2), (4100, 14336, 1), (300, 2304, 5),
-               (8200, 4096, 4), (300, 2304, 12), (1100, 4352, 40)]
+               (8200, 4096, 4), (300, 2304, 12), (1100, 4352, 40), (300, 2304, 1030)]
 # lw_matvec_multi: the fused single-token launch and the fused few-token launch.
 EDGE_MULTI = [((3000, 2000), 2048, 1), ((8200, 8200), 4096, 4)]
 KINDS = ["zero_rows", "zero_scales", "eq1_normal", "x_times_2^60", "x_times_2^-60"]

@@ -11,9 +11,14 @@ from paper_2605_20706_amd import binding, layout, synth
 from paper_2605_20706_amd.layout import F16, MXFP4, Q4_0, Q4_1, Q4_K, Q5_0, Q5_1, Q5_K, Q6_K, Q8_0
 
 # (M, K, n_tok): one row; a ragged row tile; 9 super-blocks over 8 waves; a
-# token tile and one more token; 32 tokens and one more; the most tokens
-SHAPES = [(1, 256, 9), (17, 512, 16), (65, 2304, 13), (100, 4096, 17), (130, 2048, 33), (49, 768, 128)]
-FEW = [(33, 4096, 3), (70, 6400, 6), (12300, 2048, 8)]
+# token tile and one more token; 32 tokens and one more; the most tokens; then
+# 32 and 64 rows a workgroup with 16 and 32 tokens, ragged rows and tokens
+SHAPES = [(1, 256, 9), (17, 512, 16), (65, 2304, 13), (100, 4096, 17), (130, 2048, 33), (49, 768, 128),
+          (6150, 768, 13), (12300, 768, 13), (3001, 1024, 77), (4111, 768, 99)]
+# 2 to 8 tokens (two and four pairs are loaded) with 16, 32 and 64 rows a workgroup
+FEW = [(33, 4096, 3), (70, 6400, 6), (12300, 2048, 8), (33, 2048, 4), (33, 4096, 4), (33, 512, 6), (4100, 2048, 3),
+       (6150, 4096, 3), (6150, 4096, 7), (16001, 2048, 3), (16001, 2048, 7), (12300, 2048, 4), (12300, 4096, 3),
+       (12300, 4096, 8)]
 
 
 def run_check(oracle_mod, fmt, M, K, n_tok):
@@ -60,7 +65,7 @@ def test_offsets_cancel(oracle_mod, fmt, M, K, n_tok):
     2^-24 of a partial sum that grows as the root, 2^-24 * 2, and again for the
     formats with a term of their own for the minimum."""
     import torch
-    assert binding.kernel_name(fmt, M, K, n_tok).count(",") == 4
+    assert binding.kernel_name(fmt, M, K, n_tok).startswith("kpart_kernel<")
     rng = np.random.default_rng([80, fmt])
     W = synth.gen_packed(fmt, M * K, rng)
     x = (rng.integers(2 ** 15, 2 ** 16, (n_tok, K)) * 2.0 ** -15 * rng.choice([-1, 1], (n_tok, K))).astype(np.float32)
@@ -76,7 +81,7 @@ def test_q8_0_half_super_blocks(oracle_mod, K):
     """Q8_0 with 64 rows a workgroup: units of half a super-block, fewer than
     the waves and two for some, on ragged rows and tokens."""
     M, n_tok = 1003, 401
-    assert binding.kernel_name(Q8_0, M, K, n_tok).replace(" ", "") == "gemm_kernel<1,2,4,16,2>"
+    assert binding.kernel_name(Q8_0, M, K, n_tok).replace(" ", "") == "kpart_kernel<1,2,4,16,2>"
     run_check(oracle_mod, Q8_0, M, K, n_tok)
 
 
@@ -129,7 +134,7 @@ def test_f16_all_bits(M, K, n_tok):
     returns its activations bit for bit: all 24 bits, whatever their size and
     that of the others (the smallest weight's outputs stay above 2^-126)."""
     import torch
-    assert binding.kernel_name(F16, M, K, n_tok).count(",") == 4
+    assert binding.kernel_name(F16, M, K, n_tok).startswith("kpart_kernel<")
     rng = np.random.default_rng(77)
     w = np.zeros((M, K), np.float16)
     col = rng.integers(0, K, M)
@@ -213,18 +218,30 @@ def test_q8_0_infinities_and_range(M, K, n_tok):
     assert np.isnan(y[0, 1:]).all() and (y[1:, 1:] == x[1:, col[1:]]).all()  # inf x 0: NaN
 
 
+def test_every_form_is_launched():
+    """Every instantiation that a format selects over a grid of shapes is one
+    that the shapes above launch on the GPU (no GPU here)."""
+    for fmt in layout.FORMAT_NAMES:
+        covered = {binding.kernel_name(fmt, *s) for s in SHAPES + FEW + [(1003, 768, 401)]}
+        for M in (1, 100, 1000, 3000, 4096, 6150, 8192, 9000, 12300, 14336, 16384, 20000, 33000, 65536, 128256):
+            for K in (256, 768, 1024, 1280, 2048, 2304, 3072, 4096, 6400, 8192, 14336):
+                for n_tok in (2, 3, 4, 5, 6, 8, 9, 13, 16, 17, 33, 64, 77, 100, 128, 200, 401, 700, 1000):
+                    kern = binding.kernel_name(fmt, M, K, n_tok)
+                    assert kern in covered or not kern.startswith("kpart_kernel<"), (fmt, M, K, n_tok, kern)
+
+
 def test_routes():
     """Where the rule draws its lines, and the launches of each side (no GPU)."""
     name, count = binding.kernel_name, binding.launch_count
     for fmt in layout.FORMAT_NAMES:
         if fmt != F16:
-            assert count(fmt, 4096, 4096, 16) == 1 and name(fmt, 4096, 4096, 16).count(",") == 4, fmt
+            assert count(fmt, 4096, 4096, 16) == 1 and name(fmt, 4096, 4096, 16).startswith("kpart_kernel<"), fmt
     assert name(Q8_0, 2048, 2048, 5).startswith("gemv_kernel<1, 5")      # 10240 activations: the vector kernel
-    assert name(Q8_0, 2048, 2048, 6) == "gemv_kernel<1, 1, 1, 4, 3>"     # three bf16 parts
-    assert name(F16, 2048, 2048, 3).count(",") == 3
-    assert name(F16, 2048, 2048, 4) == "gemv_kernel<0, 1, 1, 2, 3>"
+    assert name(Q8_0, 2048, 2048, 6) == "kpart_kernel<1, 1, 1, 4, 3>"     # three bf16 parts
+    assert name(F16, 2048, 2048, 3).startswith("gemv_kernel<")
+    assert name(F16, 2048, 2048, 4) == "kpart_kernel<0, 1, 1, 2, 3>"
     assert name(Q4_0, 65536, 4096, 64) == "gemm32_kernel<2, 8>"         # tall: the tiled kernel
-    assert name(Q4_0, 1024, 4096, 64) == "gemm32_kernel<2, 2, 1, 16, 2>"
+    assert name(Q4_0, 1024, 4096, 64) == "kpart_kernel<2, 2, 1, 16, 2>"
     assert name(Q4_0, 1024, 4096, 129) == "gemm32_kernel<2, 8>"
     assert name(Q4_K, 1000, 1 << 24, 12) == "gemm32_kernel<3, 8>"       # beyond 32-bit lane offsets
     assert count(F16, 2048, 2048, 34) == 2 and count(F16, 4096, 4096, 34) == 1
@@ -234,7 +251,7 @@ def test_routes_of_few_tokens():
     """Up to 8 tokens: one round of workgroups, and not a second one with little
     in it; long K over few rows stays with the pair-step kernel (no GPU)."""
     def here(fmt, M, K, n_tok):
-        return binding.kernel_name(fmt, M, K, n_tok).count(",") == 4
+        return binding.kernel_name(fmt, M, K, n_tok).startswith("kpart_kernel<")
     for n_tok in (6, 7):
         for fmt in (Q4_0, Q4_K, Q4_1):
             assert not here(fmt, 4096, 14336, n_tok) and not here(fmt, 3000, 12288, n_tok)

@@ -72,8 +72,20 @@ def test_multi_fewtok_kernel(oracle_mod, fmt, Ms, K):
     # two tokens are fused too where no register kernel takes them
     for n_tok in ((3, 8) if fmt in (Q4_0, Q4_K, Q4_1, Q1_0) else (2, 3, 8)):
         name = binding.kernel_name_multi(fmt, list(Ms), K, n_tok)
-        assert name.startswith("fewtok_kernel<%d, " % fmt), name
+        # 8048 rows in all: K split over the waves, for the formats without the pair-step kernel
+        kern = "kpart" if sum(Ms) == 8048 and fmt not in (Q4_0, Q4_K, Q4_1) else "fewtok"
+        assert name.startswith("%s_kernel<%d, " % (kern, fmt)), name
         run_multi(oracle_mod, fmt, list(Ms), K, n_tok, 34)
+
+
+@pytest.mark.parametrize("fmt", [Q4_K, Q5_0, Q5_1, Q5_K, Q6_K, Q2_K, MXFP4, Q1_0])
+def test_multi_fewtok_ragged(oracle_mod, fmt):
+    """The few-token kernel over ragged segments, a tile or more a wave."""
+    Ms, K = [9000, 9037, 2048], 512
+    for n_tok in (3, 8):
+        name = binding.kernel_name_multi(fmt, Ms, K, n_tok)
+        assert name.startswith("fewtok_kernel<%d, " % fmt), name
+        run_multi(oracle_mod, fmt, Ms, K, n_tok, 35)
 
 
 def test_multi_in_graph(oracle_mod):
