@@ -20,8 +20,10 @@ REG1 = {10: 2048, 11: 2048, 12: 2048, 13: 4096, 14: 4096, 15: 4096, 16: 4096, 17
 REG2 = {21: 2048, 22: 4096, 23: 8192, 24: 14336, 25: 4096}
 CASES = ([(c, K, 1, M) for c, K in REG1.items() for M in (17, 3001)]
          + [(c, K, 2, M) for c, K in REG2.items() for M in (5, 2500)]
-         + [(1, 4096, 1, 3001), (30, 4096, 4, 8200), (31, 2304, 5, 300), (31, 2304, 12, 300),
-            (32, 2304, 9, 300), (32, 4352, 16, 1100)])
+         + [(1, 4096, 1, 3001), (30, 4096, 4, 8200), (31, 2304, 5, 300),
+            (32, 2304, 9, 300), (32, 4352, 16, 1100)]
+         + [(33, 2304, n_tok, 300) for n_tok in (2, 5, 8, 12, 40)])
+FAMILY = {1: "gemv1_kernel", 30: "fewtok_kernel", 31: "multitok_pk_kernel", 32: "gemm32_kernel", 33: "kpart_kernel"}
 
 
 class forced:
@@ -48,6 +50,7 @@ def test_forced_candidate(oracle_mod, fmt, cand, K, n_tok, M):
     with forced(cand):
         kern = kernel_of(fmt, M, K, n_tok)
         print("cand %d fmt=%d M=%d K=%d n_tok=%d -> %s" % (cand, fmt, M, K, n_tok, kern), flush=True)
+        assert kern.split("<")[0] == FAMILY.get(cand, "gemv1r_kernel")
         y = binding.matvec(fmt, to_gpu(W), to_gpu(x), M, K)
         torch.cuda.synchronize()
     ref = Ref(oracle_mod, fmt, W, x, M, K)
