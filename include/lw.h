@@ -171,9 +171,8 @@ enum {
  * bfloat16 low part, accumulating in float32. f16 weights and, up to
  * LW_GEMV_MAX_TOK tokens, Q8_0 keep float32's precision there: activations in
  * three bfloat16 parts, which hold all 24 bits, f16 weights exactly in two;
- * results that are not finite, or below 2^-80, are formed in float32.
- * Every path's
- * error relative to sum_k |w * x| stays below 1e-4.
+ * results that are not finite, or below 2^-80, are formed in float32. Every
+ * path's error relative to sum_k |w * x| stays below 1e-4.
  */
 LW_API int lw_matvec(int fmt, const void* W, const float* x, float* y,
               int64_t M, int64_t K, int64_t n_tok, void* stream);
